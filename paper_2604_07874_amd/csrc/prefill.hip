@@ -223,10 +223,19 @@ __global__ __launch_bounds__(256, 2) void paged_prefill_attn_slice_kernel(const 
     }
     return r;
   };
-  // One 16-byte global->LDS load per lane: scalar base, 32-bit lane offset, destination in m0 (the instruction
-  // needs one wait state behind the write of m0).
+  // One 16-byte global->LDS load per lane: scalar base, 32-bit lane offset, destination in m0.  The instruction
+  // needs one wait state behind the write of m0 and five behind a vector instruction's write of its scalar base
+  // (v_readlane in blocks_of); the compiler keeps such distances for its own loads but does not look inside
+  // assembly.  So block addresses pass through one of two statements between blocks_of and their first load, both
+  // volatile, which keeps them and the loads in order: the prologue's waits the five states out (settled), and a
+  // step's, at its start, has a wait, a barrier and six LDS reads behind it before the first load.  m0 cannot be named as overwritten (it is a
+  // reserved register); the compiler keeps nothing in it and sets it ahead of each use of its own.
   auto load_lds = [&](uint32_t dst, uint64_t base, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(dst), "v"(off), "s"(base) : "memory");
+  };
+  auto settled = [&](Blocks& b0, Blocks& b1, Blocks& b2, Blocks& b3, Blocks& b4) {
+    asm volatile("s_nop 4" : "+s"(b0.b[0]), "+s"(b0.b[1]), "+s"(b1.b[0]), "+s"(b1.b[1]), "+s"(b2.b[0]), "+s"(b2.b[1]),
+                             "+s"(b3.b[0]), "+s"(b3.b[1]), "+s"(b4.b[0]), "+s"(b4.b[1]));
   };
   const uint32_t k_dst = __builtin_amdgcn_readfirstlane(lds_addr(&k_lds4[0][0]) + 4 * wave * ROW);
   const uint32_t v_dst = __builtin_amdgcn_readfirstlane(lds_addr(&v_lds4[0][0]) + 4 * wave * ROW);
@@ -318,7 +327,8 @@ __global__ __launch_bounds__(256, 2) void paged_prefill_attn_slice_kernel(const 
     const uint32_t v_slot = slot_of(grp), k_slot = slot_of(grp + 2);
     const uint32_t v_to = kFast ? ((J + 3) & 3) * SLOT : slot_of(grp + 3), k_to = kFast ? ((J + 5) & 3) * SLOT : slot_of(grp + 5);
     if ((!kFast || J == 3) && ((grp + 5) & 31) == 0) window((grp + 5) >> 5);
-    const Blocks next = blocks_of(grp + 5);
+    Blocks next = blocks_of(grp + 5);
+    asm volatile("" : "+s"(next.b[0]), "+s"(next.b[1]));   // read before what follows, see load_lds
     // K rows of group grp + 2 and V rows of group grp have landed: this wave's loads here (those of the last
     // two steps may be pending), everybody's behind the barrier
     asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
@@ -406,9 +416,10 @@ __global__ __launch_bounds__(256, 2) void paged_prefill_attn_slice_kernel(const 
   __syncthreads();   // the addresses are in LDS
   window(0);
   {
-    const Blocks b0 = blocks_of(0), b1 = blocks_of(1), b2 = blocks_of(2);
+    Blocks b0 = blocks_of(0), b1 = blocks_of(1), b2 = blocks_of(2);
     ahead1 = blocks_of(3);
     ahead2 = blocks_of(4);
+    settled(b0, b1, b2, ahead1, ahead2);
     load_k(0 * SLOT, b0, 0);
     load_k(0 * SLOT, b0, 1);
     load_k(1 * SLOT, b1, 0);
