@@ -217,8 +217,10 @@ int kv_attn_run_layer(vkv_pool* pool, int32_t layer, int32_t* cursor_slice,
  * of the library's device image (each GPU the library runs on holds its own copy
  * until the process ends).  The call allocates nothing and frees nothing, on the
  * device or through the runtime; it enqueues the attention kernel on `stream` and
- * returns (counters carry the number of the call they count for, so that nothing
- * has to be cleared first, whatever an earlier call left behind).
+ * returns.  Counters carry the number of the call they count for, so that nothing
+ * has to be cleared first, whatever an earlier call left behind; a call recorded
+ * into a graph, whose replays repeat one number, enqueues a small kernel that
+ * clears its counters ahead of the attention kernel instead.
  *   ctx_len_dev    device int32 [num_seqs], every value in [1, max_ctx_tokens]
  *   max_ctx_tokens upper bound of the context lengths, <= max_blk * 16; the grid
  *                  has one workgroup per (sequence, chunk slot, kv head), and

@@ -47,6 +47,12 @@ int static_scratch_for_current_device(void** out) {
   return VKV_OK;
 }
 
+// Ahead of a static call that is recorded into a graph: its replays all carry the number it was recorded with.
+__global__ void clear_counters_kernel(uint64_t* p, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0u;
+}
+
 static int check_bound(vkv_pool* p, const void* workspace, const char* who) {
   if (!p) { set_error("%s: null pool", who); return VKV_E_INVAL; }
   if (p->broken) { set_error("%s: pool unusable after a HIP failure", who); return VKV_E_HIP; }
@@ -581,9 +587,16 @@ int paged_decode_attn_layer_static(vkv_pool* p, int32_t layer, const void* q, co
   a.part_acc = (float*)(sc + off_acc);
   a.part_ml = (float*)(sc + off_ml);
   // Counters are tagged with the call's number instead of cleared by a kernel of their own ahead of this one
-  // (1.4-4.5 us and a launch: 24 sequences 43 us with it).
+  // (1.4-4.5 us and a launch: 24 sequences 43 us with it).  A replay of a recorded call carries the number of its
+  // recording, which calls since then have passed: recorded, the call does clear its counters (a fill kernel, not a
+  // memset node).
   a.tagged = (uint64_t*)(sc + kStaticScratchBytes);
   a.call = g_static_calls.fetch_add(1, std::memory_order_relaxed) + 1;
+  if (max_chunks > 1 && stream_capturing(hs)) {
+    const int n = num_seqs * Hkv;   // at most kStaticCounters, see there
+    hipLaunchKernelGGL(clear_counters_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, hs, a.tagged, n);
+    VKV_HIP(hipGetLastError());
+  }
   a.out = (float*)out;
   a.err = err_flag_dev ? err_flag_dev : (uint32_t*)sc;
   a.block_elems = p->block_elems;

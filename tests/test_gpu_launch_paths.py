@@ -149,6 +149,73 @@ def test_static_call_in_a_graph_between_other_calls():
         c.close()
 
 
+def _static_scratch(vkv):
+    """The static call's 16 MiB array and the counters behind it as tensors, and the number of the last call."""
+    import ctypes
+    import subprocess
+    lib = vkv.lib
+    base = ctypes.c_void_p()
+    assert lib["_ZN3vkv33static_scratch_for_current_deviceEPPv"](ctypes.byref(base)) == 0
+
+    def view(at, n, kind):
+        class View:
+            __cuda_array_interface__ = {"shape": (n,), "typestr": kind, "data": (base.value + at, False), "version": 3}
+        return torch.as_tensor(View(), device="cuda:0")
+
+    syms = {l.split()[-1]: int(l.split()[0], 16) for l in subprocess.run(
+        ["nm", lib._name], capture_output=True, text=True, check=True).stdout.splitlines() if l[0] != " "}
+    load = ctypes.cast(lib.kv_pool_init, ctypes.c_void_p).value - syms["kv_pool_init"]
+    number = next(v for k, v in syms.items() if "g_static_calls" in k)
+    return view(0, 4 << 20, "<f4"), view(16 << 20, 32768, "<i8"), lambda: ctypes.c_uint64.from_address(load + number).value
+
+
+@pytest.mark.parametrize("left_by", ["later call", "its own number"])
+def test_static_call_in_a_graph_after_counters_were_left_behind(left_by):
+    """What two overlapping calls could leave in the counters, written there by hand: every replay starts from zero
+    whatever it finds, and the calls after it too."""
+    from gpu_util import DeviceCase
+    c = DeviceCase(synth.workload("llama8b_small"), seed=15, host_pool=False)
+    try:
+        g, vkv = c.wl.geom, c.vkv
+        _, q_t = c.q_dev(1)
+        n = c.wl.num_seqs
+        ctx_t = torch.from_numpy(c.st.ctx_len).cuda()
+        top = int(c.st.ctx_len.max())
+        scratch, counters, calls = _static_scratch(vkv)
+
+        def call(out):
+            vkv.paged_decode_attn_layer_static(c.pool, 1, q_t, c.tables_t, ctx_t, top, 64, out)
+
+        want = torch.empty((n, g.num_q_heads, g.head_dim), dtype=torch.float32, device="cuda:0")
+        before = calls()
+        call(want)
+        assert calls() == before + 1
+        torch.cuda.synchronize()
+        assert not counters.any()
+        got = torch.empty_like(want)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call(got)
+        number = calls()
+        call(want)                                # a later call, with a higher number
+        assert calls() == number + 1
+        left = ((number if left_by == "its own number" else number + 1) << 16) + 1     # one chunk counted already
+        for rep in range(3):
+            for what in (graph.replay, lambda: call(got)):
+                torch.cuda.synchronize()
+                counters[:n * g.num_kv_heads].fill_(left)
+                scratch.fill_(float("nan"))       # a merge that comes too early finds no partial result
+                got.fill_(float("nan"))
+                what()
+                torch.cuda.synchronize()
+                assert torch.equal(got, want), rep
+                assert not counters.any()
+    finally:
+        torch.cuda.synchronize()
+        counters.zero_()
+        c.close()
+
+
 @pytest.mark.parametrize("groups", [1, 2, 3, 4, 5, 6, 7, 8, 9, 13, 32, 33, 37])
 @pytest.mark.parametrize("name", ["llama8b_small", "llama70b_tp8_small"])
 def test_prefill_items_of_every_small_group_count(name, groups):
