@@ -182,7 +182,9 @@ int kv_attn_check(vkv_pool* pool, void* workspace, void* stream);
 /* Slice scheduler.  Issues slices *cursor_slice .. n_slices-1 of `layer`,
  * keeping at most max_inflight (1..8) launches unfinished so that the
  * host stays close to the device; the count carries over from one call to the
- * next (use one stream per pool for these calls).  With max_inflight >= 2 and
+ * next, those of kv_prefill_run_layer included (use one stream per pool for all
+ * of them: with several every launch is still counted, but one may be taken for
+ * finished when a later one on another stream has started).  With max_inflight >= 2 and
  * all slices on one stream the launches report their start through pinned host
  * memory that the host polls, so kernels follow each other directly; otherwise
  * they report their end there, or an event is recorded behind each.  Before each slice it tests

@@ -144,28 +144,37 @@ __global__ void progress_marker_kernel(uint32_t* word, uint32_t value) {
   __hip_atomic_store(word, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-constexpr uint32_t kEndSlots = 16;   // words for launches' ends, here and in the workspace header: more than can be in flight
-static_assert(kMaxInflight < (int)kEndSlots, "a slot is used again only when its launch has been waited for");
+// Where a launch reports to: a word of its own among as many as cannot be in flight, so that neither the order in which
+// launches on two streams end nor one that starts late on a stream of its own can take back what another has reported.
+constexpr uint32_t kEndSlots = 16;   // here and in the workspace header
+constexpr uint32_t kStartSlots = 32;
+static_assert(kMaxInflight < (int)kEndSlots && kMaxInflight < (int)kStartSlots, "a slot is used again only when its launch has been waited for");
+static inline uint32_t mark_word() { return 1; }
+static inline uint32_t end_word(uint32_t n) { return 16 + n % kEndSlots; }
+static inline uint32_t start_word(uint32_t n) { return 32 + n % kStartSlots; }
 
 Report next_report(vkv_pool* p, void* header) {
   p->launched = true;
   Report r{};
-  if (!p->report_seq) return r;
-  r.seq = p->report_seq;
-  if (p->sched_mode == 2) {
-    r.started = p->progress_dev;
-  } else {
-    r.finished = p->progress_dev + 16 + r.seq % kEndSlots;
+  r.seq = p->next.number;
+  if (p->next.how == Launch::kStart) {
+    r.started = p->progress_dev + start_word(r.seq);
+  } else if (p->next.how == Launch::kEnd) {
+    r.finished = p->progress_dev + end_word(r.seq);
     r.ended = (uint32_t*)header + 16 + r.seq % kEndSlots;
   }
   return r;
 }
 
-// Waits (polling pinned host memory; no runtime call) until *word has reached `want`.  A sleep, however short, takes
-// the host 50 us and more, which would leave a stream empty for as long: launches are fractions of a millisecond
-// apart, so it spins for several of them before it gives the core away.
-static void wait_progress(const volatile uint32_t* word, uint32_t want) {
-  const auto reached = [&]() { return (int32_t)(__atomic_load_n(word, __ATOMIC_ACQUIRE) - want) >= 0; };
+static bool reported(const vkv_pool* p, uint32_t word, uint32_t want) {
+  return (int32_t)(__atomic_load_n(p->progress_host + word, __ATOMIC_ACQUIRE) - want) >= 0;
+}
+
+// Waits until `reached`, polling pinned host memory (no runtime call).  A sleep, however short, takes the host 50 us and
+// more, which would leave a stream empty for as long: launches are fractions of a millisecond apart, so it spins for
+// several of them before it gives the core away.
+template <typename Reached>
+static void wait_progress(Reached reached) {
   if (reached()) return;
   const auto spin_until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
   do {
@@ -177,22 +186,63 @@ static void wait_progress(const volatile uint32_t* word, uint32_t want) {
   while (!reached()) std::this_thread::sleep_for(std::chrono::microseconds(2));
 }
 
+// The end of a launch that reports its start is seen when the next one has started behind it.  Where none will, because
+// what comes now is counted otherwise (`last`) or the next one went to another stream, a one-thread kernel behind
+// everything enqueued on `hs` so far says so.
+static int mark_starts(vkv_pool* p, hipStream_t hs, bool last) {
+  Launch *newest = nullptr, *here = nullptr;   // of the launches that report their start; of those on this stream
+  for (int i = 0; i < p->inflight_count; ++i) {
+    Launch* l = &p->inflight[(p->inflight_head + i) % kMaxInflight];
+    if (l->how != Launch::kStart) continue;
+    newest = l;
+    if (l->on == hs) here = l;
+  }
+  Launch* open[2] = {here != newest ? here : nullptr, last ? newest : nullptr};
+  for (Launch* l : open) {
+    if (!l || l->mark) continue;
+    const uint32_t mark = ++p->mark_seq;
+    hipLaunchKernelGGL(progress_marker_kernel, dim3(1), dim3(1), 0, hs, p->progress_dev + mark_word(), mark);
+    VKV_HIP(hipGetLastError());
+    l->mark = mark;
+  }
+  return VKV_OK;
+}
+
+// waits for the end of the oldest launch in flight and takes it off the ring
+static int retire_oldest(vkv_pool* p) {
+  const Launch l = p->inflight[p->inflight_head];
+  if (l.how == Launch::kStart) {
+    wait_progress([&]() {
+      return reported(p, start_word(l.number + 1), l.number + 1) || (l.mark && reported(p, mark_word(), l.mark));
+    });
+  } else if (l.how == Launch::kEnd) {
+    wait_progress([&]() { return reported(p, end_word(l.number), l.number); });
+  } else {
+    VKV_HIP(hipEventSynchronize(p->inflight_ev[p->inflight_head]));
+  }
+  p->inflight_head = (p->inflight_head + 1) % kMaxInflight;
+  --p->inflight_count;
+  return VKV_OK;
+}
+
 // Slice scheduler shared by decode and prefill: issues steps *cursor .. n_slices + n_tail - 1
 // (slices through `launch`, then n_tail follow-up steps through `tail`, all on the caller's
 // stream; tail_launches false: the follow-up steps have nothing to do), keeping at most
 // max_inflight launches unfinished; that state persists across calls.  Stops at a step boundary
 // when the yield flag is set.
-// How the lead over the GPU is bounded (an event record between two kernels costs 10-14 us of GPU time, and the host
-// another 10 us or so to see it, so mostly without events):
+// How the lead over the GPU is bounded: the launches that may be unfinished stand in one ring, oldest first, across
+// calls and whatever layers they belong to, and a launch goes out once fewer than max_inflight are left in it.  How the
+// end of one is seen differs (an event record between two kernels costs 10-14 us of GPU time, and the host another 10 us
+// or so to see it, so mostly without events):
 //   - reports of the start (one stream, max_inflight >= 2): every launch stores its number in pinned host memory
-//     when it starts, i.e. when all earlier launches of the stream have finished, and the host
-//     enqueues launch n once launch n - max_inflight + 1 has started; kernels follow each other with
-//     nothing in between.  A drain enqueues a one-thread marker kernel behind the last launch and
-//     polls for it.
+//     when it starts, i.e. when all earlier launches of the stream have finished; kernels follow each other with
+//     nothing in between.  Where no launch of this kind follows (a yield, a call that counts otherwise) a one-thread
+//     marker kernel behind it reports instead.
 //   - reports of the end (two streams, where a launch's start says nothing about the other stream's,
-//     and max_inflight 1): the last workgroup of a launch stores its number, and the host enqueues a
-//     launch when the one max_inflight back has ended.  (A one-thread kernel behind every launch in
-//     its place had to wait for registers on a full chip: 32 prompts 2008 us against 1893 with events.)
+//     and max_inflight 1): the last workgroup of a launch stores its number.  (A one-thread kernel behind every launch in
+//     its place had to wait for registers on a full chip: 32 prompts 2008 us against 1893 with events.  On one stream
+//     in place of reports of the start the workgroups' tickets cost a short layer more than they save: 48 sequences of
+//     head dim 64 92 : 110 us, 64 of the 8B shape 431 : 436.)
 //   - events (end_events: decode on two streams): a launch that goes out the moment the one two back has ended
 //     shares the chip with the one between them from start to end, and both run dry together; the 25 us that an
 //     event takes to be seen keep the two streams half a launch apart (ten 18 GB layers in 17 slices: decode 6129-6254
@@ -214,27 +264,14 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
   int st = VKV_OK;
   const bool two = p->overlap && p->aux_stream && max_inflight >= 2 && may_overlap && n_slices - *cursor >= 2;
   const bool capturing = stream_capturing(hs);
-  const int mode = !two && max_inflight >= 2 ? 2 : two && end_events ? 3 : 1;
-  auto wait_finished = [&](uint32_t n) { wait_progress(p->progress_host + 16 + n % kEndSlots, n); };
-  // every launch so far has finished; with `idle`, the GPU has nothing left to do for them either
-  auto drain = [&](bool idle) -> int {
-    if (p->sched_mode == 2) {
-      // a marker behind everything enqueued so far; it runs when the last launch has finished
-      const uint32_t mark = ++p->drain_seq;
-      hipLaunchKernelGGL(progress_marker_kernel, dim3(1), dim3(1), 0, hs, p->progress_dev + 1, mark);
-      VKV_HIP(hipGetLastError());
-      wait_progress(p->progress_host + 1, mark);
-    } else if (p->sched_mode == 3) {
-      for (; p->inflight_count > 0; --p->inflight_count, p->inflight_head = (p->inflight_head + 1) % p->inflight_cap)
-        VKV_HIP(hipEventSynchronize(p->inflight_ev[p->inflight_head]));
-      p->inflight_head = 0;
-    } else {
-      for (uint32_t n = p->finish_seq > kMaxInflight ? p->finish_seq - kMaxInflight : 0; n < p->finish_seq; ++n)
-        wait_finished(n + 1);
-    }
-    if (!idle && p->sched_mode != 2) return VKV_OK;
+  const Launch::How how = !two && max_inflight >= 2 ? Launch::kStart : two && end_events ? Launch::kEvent : Launch::kEnd;
+  // every launch so far has finished, and the GPU has nothing left to do for them
+  auto drain = [&]() -> int {
+    int r = mark_starts(p, hs, true);
+    while (r == VKV_OK && p->inflight_count > 0) r = retire_oldest(p);
+    if (r != VKV_OK) return r;
     // the slices are done, the last kernel is about to retire: the streams are idle a moment later
-    for (hipStream_t s : {hs, p->sched_mode == 2 ? hs : p->aux_stream}) {
+    for (hipStream_t s : {hs, p->aux_stream}) {
       if (s == nullptr && s != hs) continue;
       for (;;) {
         const hipError_t q = hipStreamQuery(s);
@@ -246,17 +283,10 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
     return VKV_OK;
   };
 
-  if (!capturing) {
-    if (mode == 3)
-      for (int i = 0; i < max_inflight; ++i)
-        if (!p->inflight_ev[i]) VKV_HIP(hipEventCreateWithFlags(&p->inflight_ev[i], hipEventDisableTiming));
-    if (p->sched_mode != mode || (mode == 3 && p->inflight_cap != max_inflight)) {
-      // another way of counting from here on: nothing of the old way may be left in flight
-      if (p->sched_mode != 0 && (st = drain(false)) != VKV_OK) return st;
-      p->sched_mode = mode;
-      p->inflight_cap = max_inflight;
-    }
-  }
+  if (!capturing && how == Launch::kEvent)
+    for (auto& e : p->inflight_ev)
+      if (!e) VKV_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  if (!capturing && (st = mark_starts(p, hs, how != Launch::kStart)) != VKV_OK) return st;
 
   int32_t recorded = 0;
   // one more launch may be enqueued once fewer than max_inflight are unfinished
@@ -266,36 +296,26 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
       set_error("%s: more than max_inflight launches cannot be recorded into a graph", who);
       return VKV_E_HIP;
     }
-    if (mode == 2) {
-      // launch n may go once launch n - max_inflight + 1 has started: then at most max_inflight - 1
-      // earlier launches are unfinished (one of them running)
-      const uint32_t n = p->launch_seq + 1;
-      if (n > (uint32_t)(max_inflight - 1)) wait_progress(p->progress_host, n - (uint32_t)(max_inflight - 1));
-    } else if (mode == 3) {
-      if (p->inflight_count == max_inflight) {
-        VKV_HIP(hipEventSynchronize(p->inflight_ev[p->inflight_head]));
-        p->inflight_head = (p->inflight_head + 1) % max_inflight;
-        --p->inflight_count;
-      }
-    } else {
-      const uint32_t n = p->finish_seq + 1;
-      if (n > (uint32_t)max_inflight) wait_finished(n - (uint32_t)max_inflight);
+    while (p->inflight_count >= max_inflight) {
+      const int r = retire_oldest(p);
+      if (r != VKV_OK) return r;
     }
     return VKV_OK;
   };
-  // runs one step's launch; the number it reports is taken back if it had nothing to launch
+  // runs one step's launch and counts it, unless it had nothing to launch
   auto enqueue = [&](const std::function<int()>& what, hipStream_t on) -> int {
     p->launched = false;
-    p->report_seq = capturing || mode == 3 ? 0 : (mode == 2 ? p->launch_seq : p->finish_seq) + 1;
+    if (!capturing)
+      p->next = Launch{how, how == Launch::kStart ? p->start_seq + 1 : how == Launch::kEnd ? p->end_seq + 1 : 0, 0, on};
     const int r = what();
-    p->report_seq = 0;
+    const Launch l = p->next;
+    p->next = Launch{};
     if (r != VKV_OK || !p->launched || capturing) return r;
-    if (mode == 3) {
-      VKV_HIP(hipEventRecord(p->inflight_ev[(p->inflight_head + p->inflight_count) % max_inflight], on));
-      ++p->inflight_count;
-      return VKV_OK;
-    }
-    ++(mode == 2 ? p->launch_seq : p->finish_seq);
+    const int at = (p->inflight_head + p->inflight_count) % kMaxInflight;
+    if (how == Launch::kEvent) VKV_HIP(hipEventRecord(p->inflight_ev[at], on));
+    else ++(how == Launch::kStart ? p->start_seq : p->end_seq);
+    p->inflight[at] = l;
+    ++p->inflight_count;
     return VKV_OK;
   };
   bool aux_used = false;
@@ -314,7 +334,7 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
     return VKV_OK;
   };
   auto yielded = [&](int32_t at) -> int {
-    int r = capturing ? VKV_OK : drain(true);
+    int r = capturing ? VKV_OK : drain();
     if (r != VKV_OK) return r;
     if ((r = join()) != VKV_OK) return r;
     *cursor = at;

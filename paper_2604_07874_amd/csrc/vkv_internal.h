@@ -107,6 +107,19 @@ __device__ __forceinline__ void report_end(const Report& r, uint32_t ticket) {
   }
 }
 
+// A launch that may not have finished yet, and how its end is seen.
+struct Launch {
+  enum How : int32_t {
+    kNone,
+    kStart,   // it reports its start: the next launch that does has started behind it, or marker `mark` has run
+    kEnd,     // it reports its end
+    kEvent    // an event is recorded behind it
+  } how = kNone;
+  uint32_t number = 0;   // among the launches that report the same thing
+  uint32_t mark = 0;     // number of the marker kernel behind it, 0 = none
+  hipStream_t on = nullptr;
+};
+
 // Pinned host memory that the device is given a copy of.  A small kernel reads it over the link and writes the
 // device copy, and each of its workgroups reports in pinned memory when it has read its share: a copy command with an
 // event behind it, to know when the buffer may be written again, kept the stream's next kernel waiting for 15-20 us.
@@ -226,9 +239,10 @@ struct vkv_pool {
   hipEvent_t grace_ev = nullptr;
 
   // slice scheduler
-  // ring of events behind decode launches on two streams that may still be running; it persists across calls
-  hipEvent_t inflight_ev[vkv::kMaxInflight] = {};
-  int inflight_head = 0, inflight_count = 0, inflight_cap = 0;
+  // ring of the launches that may still be running, oldest first; it persists across calls
+  vkv::Launch inflight[vkv::kMaxInflight];
+  hipEvent_t inflight_ev[vkv::kMaxInflight] = {};   // behind the launch in the same place, where it is one for which events are used
+  int inflight_head = 0, inflight_count = 0;
   // second stream for overlapping consecutive slices of one layer (created on first use)
   bool overlap = false;
   hipStream_t aux_stream = nullptr;
@@ -236,18 +250,17 @@ struct vkv_pool {
   std::atomic<int> yield_flag{0};
   // Progress words in pinned host memory that launches report to, so that the scheduler can bound
   // its lead over the GPU without an event between every two launches (an event record keeps the
-  // next kernel from starting for several microseconds): word 0 = number of the newest launch that
-  // has started, word 1 = number of the newest drain marker that has run, word 16 + n % 16 = number n
-  // of a launch that has ended (two streams: launches end in any order).
+  // next kernel from starting for several microseconds): word 1 = number of the newest marker that has run,
+  // word 16 + n % 16 = number n of a launch that has ended (two streams: launches end in any order),
+  // word 32 + n % 32 = number n of a launch that has started.
   volatile uint32_t* progress_host = nullptr;
   void* progress_block = nullptr;   // the allocation that holds them, freed with the pool
   uint32_t* progress_dev = nullptr;
-  uint32_t launch_seq = 0;       // launches numbered so far that report their start
-  uint32_t finish_seq = 0;       // launches numbered so far that report their end
-  uint32_t drain_seq = 0;        // drain markers numbered so far
-  uint32_t report_seq = 0;       // number the next launch reports, 0 = none
+  uint32_t start_seq = 0;        // launches numbered so far that report their start
+  uint32_t end_seq = 0;          // launches numbered so far that report their end
+  uint32_t mark_seq = 0;         // markers numbered so far
+  vkv::Launch next;              // what the next launch reports, kNone between the scheduler's launches
   bool launched = false;         // set by whatever the scheduler calls to enqueue a kernel
-  int sched_mode = 0;            // what bounds the lead now: 0 nothing yet, 1 reports of the end, 2 reports of the start, 3 events
 
   // per-launch timing (kv_profile_enable)
   std::vector<hipEvent_t> prof_ev;      // 2 per record: start, end
