@@ -172,18 +172,33 @@ static bool reported(const vkv_pool* p, uint32_t word, uint32_t want) {
 
 // Waits until `reached`, polling pinned host memory (no runtime call).  A sleep, however short, takes the host 50 us and
 // more, which would leave a stream empty for as long: launches are fractions of a millisecond apart, so it spins for
-// several of them before it gives the core away.
+// several of them before it gives the core away.  From then on it also asks the runtime every millisecond: a stream
+// that has failed reports nothing any more, and one that has come to its end has finished what was waited for.
 template <typename Reached>
-static void wait_progress(Reached reached) {
-  if (reached()) return;
-  const auto spin_until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+static int wait_progress(const vkv_pool* p, hipStream_t hs, Reached reached) {
+  using clk = std::chrono::steady_clock;
+  if (reached()) return VKV_OK;
+  auto ask = clk::now() + std::chrono::milliseconds(2);
   do {
     for (int i = 0; i < 64; ++i) {
-      if (reached()) return;
+      if (reached()) return VKV_OK;
       __builtin_ia32_pause();
     }
-  } while (std::chrono::steady_clock::now() < spin_until);
-  while (!reached()) std::this_thread::sleep_for(std::chrono::microseconds(2));
+  } while (clk::now() < ask);
+  while (!reached()) {
+    std::this_thread::sleep_for(std::chrono::microseconds(2));
+    if (clk::now() < ask) continue;
+    ask = clk::now() + std::chrono::milliseconds(1);
+    bool idle = true;
+    for (hipStream_t s : {hs, p->aux_stream}) {
+      if (s == nullptr && s != hs) continue;
+      const hipError_t q = hipStreamQuery(s);
+      if (q == hipErrorNotReady) idle = false;
+      else if (q != hipSuccess) return hip_fail(q, "hipStreamQuery, waiting for a launch");
+    }
+    if (idle) return VKV_OK;
+  }
+  return VKV_OK;
 }
 
 // The end of a launch that reports its start is seen when the next one has started behind it.  Where none will, because
@@ -209,17 +224,18 @@ static int mark_starts(vkv_pool* p, hipStream_t hs, bool last) {
 }
 
 // waits for the end of the oldest launch in flight and takes it off the ring
-static int retire_oldest(vkv_pool* p) {
+static int retire_oldest(vkv_pool* p, hipStream_t hs) {
   const Launch l = p->inflight[p->inflight_head];
-  if (l.how == Launch::kStart) {
-    wait_progress([&]() {
+  int st = VKV_OK;
+  if (l.how == Launch::kStart)
+    st = wait_progress(p, hs, [&]() {
       return reported(p, start_word(l.number + 1), l.number + 1) || (l.mark && reported(p, mark_word(), l.mark));
     });
-  } else if (l.how == Launch::kEnd) {
-    wait_progress([&]() { return reported(p, end_word(l.number), l.number); });
-  } else {
+  else if (l.how == Launch::kEnd)
+    st = wait_progress(p, hs, [&]() { return reported(p, end_word(l.number), l.number); });
+  else
     VKV_HIP(hipEventSynchronize(p->inflight_ev[p->inflight_head]));
-  }
+  if (st != VKV_OK) return st;
   p->inflight_head = (p->inflight_head + 1) % kMaxInflight;
   --p->inflight_count;
   return VKV_OK;
@@ -268,7 +284,7 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
   // every launch so far has finished, and the GPU has nothing left to do for them
   auto drain = [&]() -> int {
     int r = mark_starts(p, hs, true);
-    while (r == VKV_OK && p->inflight_count > 0) r = retire_oldest(p);
+    while (r == VKV_OK && p->inflight_count > 0) r = retire_oldest(p, hs);
     if (r != VKV_OK) return r;
     // the slices are done, the last kernel is about to retire: the streams are idle a moment later
     for (hipStream_t s : {hs, p->aux_stream}) {
@@ -297,7 +313,7 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
       return VKV_E_HIP;
     }
     while (p->inflight_count >= max_inflight) {
-      const int r = retire_oldest(p);
+      const int r = retire_oldest(p, hs);
       if (r != VKV_OK) return r;
     }
     return VKV_OK;

@@ -43,10 +43,31 @@ int stage_wait(Staging& s) {
     VKV_HIP(hipEventSynchronize(s.ev));
     s.ev_pending = false;
   }
+  // After a moment the runtime is asked too: a stream that has failed never reports.  One that has come to its end, or
+  // is there no longer, has nothing left that could; what it reported may take a moment to be seen.
+  using clk = std::chrono::steady_clock;
+  constexpr auto kAskEvery = std::chrono::milliseconds(1), kLetArrive = std::chrono::milliseconds(1000);
+  auto ask = clk::now() + kAskEvery;
+  clk::time_point done{};
   for (int i = 0; i < s.n_flags; ++i)
     for (int spins = 0; __atomic_load_n(&s.flags[i], __ATOMIC_ACQUIRE) != s.seq; ++spins) {
-      if (spins < 4096) __builtin_ia32_pause();
-      else std::this_thread::sleep_for(std::chrono::microseconds(2));
+      if (spins < 4096) {
+        __builtin_ia32_pause();
+        continue;
+      }
+      std::this_thread::sleep_for(std::chrono::microseconds(2));
+      const auto now = clk::now();
+      if (now < ask || stream_capturing(s.on)) continue;   // a stream being captured must not be asked
+      ask = now + kAskEvery;
+      const hipError_t q = hipStreamQuery(s.on);
+      if (q == hipErrorNotReady) continue;
+      if (q != hipSuccess && q != hipErrorInvalidHandle && q != hipErrorContextIsDestroyed)
+        return hip_fail(q, "hipStreamQuery, waiting for an upload");
+      if (done == clk::time_point{}) done = now;
+      if (now - done > kLetArrive) {
+        set_error("an upload enqueued earlier has not run, though its stream has come to its end");
+        return VKV_E_HIP;
+      }
     }
   s.n_flags = 0;
   return VKV_OK;
@@ -98,7 +119,8 @@ int ensure_plan_stage(vkv_pool* p, size_t bytes) {
 
 __global__ __launch_bounds__(256) void stage_upload_kernel(UploadShare u) { upload_share(u, blockIdx.x, gridDim.x); }
 
-UploadShare stage_begin_upload(Staging& s, void* dst, size_t bytes, int* workgroups) {
+UploadShare stage_begin_upload(Staging& s, void* dst, size_t bytes, hipStream_t on, int* workgroups) {
+  s.on = on;
   s.n_flags = (int)std::min<size_t>(Staging::kMaxFlags, std::max<size_t>(1, (bytes + 4095) / 4096));
   *workgroups = s.n_flags;
   return UploadShare{s.dev, (char*)dst, (uint64_t)bytes, s.flags_dev, ++s.seq};
@@ -113,7 +135,7 @@ int stage_upload(Staging& s, void* dst, size_t bytes, hipStream_t st) {
     return VKV_OK;
   }
   int n = 0;
-  const UploadShare u = stage_begin_upload(s, dst, bytes, &n);
+  const UploadShare u = stage_begin_upload(s, dst, bytes, st, &n);
   hipLaunchKernelGGL(stage_upload_kernel, dim3((unsigned)n), dim3(256), 0, st, u);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {

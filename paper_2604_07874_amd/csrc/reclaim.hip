@@ -232,7 +232,7 @@ int kv_reclaim_range(vkv_pool* p, int32_t lo, int32_t hi, int32_t* tables, int64
       std::copy(src.begin(), src.end(), moves.src);
       std::copy(dst.begin(), dst.end(), moves.dst);
       int n_upload = 0;
-      const UploadShare u = stage_begin_upload(p->remap, remap_dev, (size_t)nb * 4, &n_upload);
+      const UploadShare u = stage_begin_upload(p->remap, remap_dev, (size_t)nb * 4, cs, &n_upload);
       const uint32_t n_copy = (uint32_t)src.size() * pieces;
       hipLaunchKernelGGL(large ? kv_block_relocate_listed_kernel<kCopyUnrollLarge> : kv_block_relocate_listed_kernel<kCopyUnrollSmall>,
                          dim3(n_copy + (unsigned)n_upload), dim3(kCopyThreads), 0, cs, (u32x4*)p->cfg.base, n_copy, pieces,

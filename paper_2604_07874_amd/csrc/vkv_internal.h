@@ -132,6 +132,7 @@ struct Staging {
   uint32_t* flags_dev = nullptr;
   uint32_t seq = 0;
   int n_flags = 0;                          // workgroups of the upload in flight, 0 = none
+  hipStream_t on = nullptr;                 // the stream it went to
   hipEvent_t ev = nullptr;                  // uploads recorded into a graph are copy commands, waited for by event
   bool ev_pending = false;
 };
@@ -150,7 +151,7 @@ struct UploadShare {
   uint32_t* flags;
   uint32_t seq;
 };
-UploadShare stage_begin_upload(Staging& s, void* dst, size_t bytes, int* workgroups);
+UploadShare stage_begin_upload(Staging& s, void* dst, size_t bytes, hipStream_t on, int* workgroups);
 // Bound by the link's latency (one trip for the sizes of plans and remaps); 4 KiB per workgroup and trip.
 __device__ __forceinline__ void upload_share(const UploadShare& u, uint32_t block, uint32_t grid) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

@@ -82,6 +82,7 @@ void wait_idle(hipStream_t s) {
 
 hipStream_t handle(int n) { return (hipStream_t)(uintptr_t)(0x1000 + 64 * n); }
 
+bool drop_uploads = false;
 int pause_us = 0;   // how long a launch takes, 0 = as short as it gets
 
 // what a slice kernel does for the scheduler
@@ -252,6 +253,49 @@ void late_start() {
   }
 }
 
+void fail(hipStream_t s, hipError_t e) {
+  std::lock_guard<std::mutex> lock(mu);
+  stream(s)->failed = e;
+  stream(s)->open = false;
+}
+
+// A stream that fails reports nothing any more: the call that waits for it, or for an upload on it, says so.
+void failed_stream() {
+  for (int max_inflight : {1, 2}) {
+    vkv_pool* p = make_pool();
+    const hipStream_t s = handle(max_inflight);
+    CHECK(run(p, s, 2, max_inflight) == VKV_OK);
+    wait_idle(s);
+    fail(s, hipErrorLaunchFailure);
+    CHECK(run(p, s, 4, max_inflight) == VKV_E_HIP);
+    CHECK(std::strstr(vkv_last_error(), "hipStreamQuery"));
+    CHECK(kv_yield_request(p) == VKV_OK);
+    CHECK(run(p, s, 4, max_inflight) == VKV_E_HIP);
+  }
+  vkv_pool* p = make_pool();
+  static char to[4096];
+  CHECK(stage_upload(p->stage, to, sizeof to, handle(3)) == VKV_OK);
+  CHECK(ensure_plan_stage(p, 64) == VKV_OK);
+  fail(handle(3), hipErrorLaunchFailure);
+  CHECK(stage_upload(p->stage, to, sizeof to, handle(3)) == VKV_OK);
+  CHECK(ensure_plan_stage(p, 64) == VKV_E_HIP);
+  // a kernel that never ran on a stream that has nothing left to do
+  p = make_pool();
+  drop_uploads = true;
+  CHECK(stage_upload(p->stage, to, sizeof to, handle(4)) == VKV_OK);
+  CHECK(ensure_plan_stage(p, 64) == VKV_E_HIP);
+}
+
+// Long waits end where the work does, however long it takes.
+void long_waits() {
+  vkv_pool* p = make_pool();
+  pause_us = 12000;
+  for (int max_inflight : {1, 2, 3}) CHECK(run(p, handle(0), 6, max_inflight) == VKV_OK);
+  static char to[4096];
+  CHECK(stage_upload(p->stage, to, sizeof to, handle(0)) == VKV_OK);
+  CHECK(ensure_plan_stage(p, 64) == VKV_OK && unfinished == 0);
+}
+
 }  // namespace
 
 // ---- the runtime functions the library calls ----
@@ -271,8 +315,17 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   configs.pop_back();
   return hipSuccess;
 }
-// the only kernel the scheduler launches by itself: one thread that stores a number
+// the kernels launched here: an upload by workgroups of 256, and one thread that stores a number
 hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size_t, hipStream_t s) {
+  if (block.x == 256) {
+    const UploadShare u = *(UploadShare*)args[0];
+    push(s, [u, grid]() {
+      if (drop_uploads) return;
+      std::memcpy(u.dst, u.src, u.bytes);
+      for (unsigned i = 0; i < grid.x; ++i) __atomic_store_n(u.flags + i, u.seq, __ATOMIC_RELEASE);
+    });
+    return hipSuccess;
+  }
   CHECK(grid.x == 1 && block.x == 1);
   uint32_t* word = *(uint32_t**)args[0];
   const uint32_t value = *(uint32_t*)args[1];
@@ -350,7 +403,7 @@ hipError_t hipEventSynchronize(hipEvent_t e) {
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"bound", bound}, {"lower_limit", lower_limit}, {"taking_turns", taking_turns}, {"yield_between", yield_between},
-      {"late_start", late_start}};
+      {"late_start", late_start}, {"failed_stream", failed_stream}, {"long_waits", long_waits}};
   if (argc != 2 || !checks.count(argv[1])) return 2;
   checks.at(argv[1])();
   std::printf("%s holds\n", argv[1]);

@@ -23,7 +23,8 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["bound", "lower_limit", "taking_turns", "yield_between", "late_start"])
+@pytest.mark.parametrize("check", ["bound", "lower_limit", "taking_turns", "yield_between", "late_start", "failed_stream",
+                                   "long_waits"])
 def test_scheduler(program, check):
     try:
         res = subprocess.run([program, check], capture_output=True, text=True, timeout=30)
