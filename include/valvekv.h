@@ -152,7 +152,12 @@ int kv_attn_plan_read(vkv_pool* pool, int32_t* work_out_host, int32_t* slice_sta
  * slices of a layer.  A layer that was started must be finished (all its
  * slices run) before another layer uses the workspace; to abandon a layer,
  * bind again.  Blocks the host only if an earlier upload from the same pool is
- * still in flight.  Errors: VKV_E_INVAL, VKV_E_STATE (no plan), VKV_E_HIP. */
+ * still in flight.  Better done ahead of a graph capture than inside one: a bind
+ * recorded into a graph copies, at every replay, what the pool's staging buffer
+ * holds at that time, so no other plan may be bound on the pool (decode or
+ * prefill) while the graph is in use, and the buffer has to be large enough
+ * before the capture begins (bind a plan of that size once).
+ * Errors: VKV_E_INVAL, VKV_E_STATE (no plan), VKV_E_HIP. */
 int kv_attn_bind(vkv_pool* pool, void* workspace, uint64_t workspace_bytes, void* stream);
 
 /* Enqueues one slice of one layer: for every work item of the slice, scores
@@ -195,7 +200,8 @@ int kv_attn_check(vkv_pool* pool, void* workspace, void* stream);
  * without recomputing anything (the paper's requirement that preempted work is
  * resumed, not repeated: Section 2.2 on duplicated iterations; Section 4.1).
  * On VKV_OK *cursor_slice = n_slices and every slice has been enqueued (not
- * waited for).
+ * waited for).  Recorded into a graph the layer is recorded whole, whatever
+ * max_inflight says, and replays do not count towards it.
  * A layer of four slices or more is merged differently from what
  * paged_decode_attn_slice does on its own: its slices store their partial
  * results only, and one small launch behind the layer's last slice (enqueued

@@ -267,8 +267,8 @@ static int retire_oldest(vkv_pool* p, hipStream_t hs) {
 // into the caller's stream inside this call), so the workgroups of the next slice fill the
 // compute units the tail of the previous one leaves idle; slices of one layer are independent
 // (results are merged through per-item partials), so their order does not matter.
-// Recorded into a graph nothing runs, so nothing can be waited for: up to max_inflight launches per
-// call, without reports.
+// Recorded into a graph nothing runs, so there is nothing to wait for and nothing to report: the whole
+// layer is recorded, and its replays do not count.
 int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_inflight, hipStream_t hs,
                const char* who, const std::function<int(int32_t, hipStream_t)>& launch, int32_t n_tail,
                const std::function<int(int32_t)>& tail, bool tail_launches, bool may_overlap, bool end_events,
@@ -304,14 +304,9 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
       if (!e) VKV_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   if (!capturing && (st = mark_starts(p, hs, how != Launch::kStart)) != VKV_OK) return st;
 
-  int32_t recorded = 0;
   // one more launch may be enqueued once fewer than max_inflight are unfinished
   auto admit = [&]() -> int {
-    if (capturing) {
-      if (recorded++ < max_inflight) return VKV_OK;
-      set_error("%s: more than max_inflight launches cannot be recorded into a graph", who);
-      return VKV_E_HIP;
-    }
+    if (capturing) return VKV_OK;
     while (p->inflight_count >= max_inflight) {
       const int r = retire_oldest(p, hs);
       if (r != VKV_OK) return r;
@@ -349,21 +344,26 @@ int run_slices(vkv_pool* p, int32_t* cursor, int32_t n_slices, int32_t max_infli
     }
     return VKV_OK;
   };
+  // also after a failure: whoever waits for the caller's stream has waited for what went to the second one
+  auto leave = [&](int r) -> int {
+    const std::string why = r < 0 ? vkv_last_error() : "";
+    const int j = join();
+    if (r < 0) set_error("%s", why.c_str());   // the first failure is the one to tell
+    return r < 0 ? r : j != VKV_OK ? j : r;
+  };
   auto yielded = [&](int32_t at) -> int {
-    int r = capturing ? VKV_OK : drain();
-    if (r != VKV_OK) return r;
-    if ((r = join()) != VKV_OK) return r;
-    *cursor = at;
-    return VKV_YIELDED;
+    const int r = leave(capturing ? VKV_YIELDED : (st = drain()) != VKV_OK ? st : VKV_YIELDED);
+    if (r == VKV_YIELDED) *cursor = at;
+    return r;
   };
   for (int32_t s = *cursor; s < n_slices; ++s) {
     if (p->yield_flag.load(std::memory_order_acquire)) return yielded(s);
     const hipStream_t on = (two && (s & 1)) ? p->aux_stream : hs;
-    if ((st = admit()) != VKV_OK) return st;
+    if ((st = admit()) != VKV_OK) return leave(st);
     // admit() may have waited for up to one slice: a request that came in meanwhile is honoured now
     if (p->yield_flag.load(std::memory_order_acquire)) return yielded(s);
-    if ((st = enqueue([&]() { return launch(s, on); }, on)) != VKV_OK) return st;
     if (on != hs) aux_used = true;
+    if ((st = enqueue([&]() { return launch(s, on); }, on)) != VKV_OK) return leave(st);
     // what belongs behind the last slice goes out with it, on the caller's stream, once the second
     // stream's slices are joined: no yield test lies between the two
     if (s == n_slices - 1 && after_slices) {

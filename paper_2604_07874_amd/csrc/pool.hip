@@ -39,10 +39,6 @@ bool stream_capturing(hipStream_t st) {
 }
 
 int stage_wait(Staging& s) {
-  if (s.ev_pending) {
-    VKV_HIP(hipEventSynchronize(s.ev));
-    s.ev_pending = false;
-  }
   // After a moment the runtime is asked too: a stream that has failed never reports.  One that has come to its end, or
   // is there no longer, has nothing left that could; what it reported may take a moment to be seen.
   using clk = std::chrono::steady_clock;
@@ -75,7 +71,6 @@ int stage_wait(Staging& s) {
 
 void stage_free(Staging& s) {
   if (s.host) (void)hipHostFree(s.host);
-  if (s.ev) (void)hipEventDestroy(s.ev);
   s = Staging{};
 }
 
@@ -128,10 +123,8 @@ UploadShare stage_begin_upload(Staging& s, void* dst, size_t bytes, hipStream_t 
 
 int stage_upload(Staging& s, void* dst, size_t bytes, hipStream_t st) {
   if (stream_capturing(st)) {
-    if (!s.ev) VKV_HIP(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
+    // a replay cannot be waited for from here: what the buffer holds then is the caller's affair
     VKV_HIP(hipMemcpyAsync(dst, s.host, bytes, hipMemcpyHostToDevice, st));
-    VKV_HIP(hipEventRecord(s.ev, st));
-    s.ev_pending = true;
     return VKV_OK;
   }
   int n = 0;

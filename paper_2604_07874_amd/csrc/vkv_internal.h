@@ -123,6 +123,7 @@ struct Launch {
 // Pinned host memory that the device is given a copy of.  A small kernel reads it over the link and writes the
 // device copy, and each of its workgroups reports in pinned memory when it has read its share: a copy command with an
 // event behind it, to know when the buffer may be written again, kept the stream's next kernel waiting for 15-20 us.
+// Recorded into a graph an upload is a copy command, which reads the buffer at every replay.
 struct Staging {
   static constexpr int kMaxFlags = 128;      // workgroups of an upload
   char* host = nullptr;                     // data
@@ -133,8 +134,6 @@ struct Staging {
   uint32_t seq = 0;
   int n_flags = 0;                          // workgroups of the upload in flight, 0 = none
   hipStream_t on = nullptr;                 // the stream it went to
-  hipEvent_t ev = nullptr;                  // uploads recorded into a graph are copy commands, waited for by event
-  bool ev_pending = false;
 };
 int stage_wait(Staging& s);                              // the buffer may be written again
 // waits, and makes room: `cap` bytes (at least `bytes`) and the flags, `behind` more bytes after them; a block that is

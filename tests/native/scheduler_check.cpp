@@ -296,6 +296,53 @@ void long_waits() {
   CHECK(ensure_plan_stage(p, 64) == VKV_OK && unfinished == 0);
 }
 
+// Recorded into a graph a layer of any length goes through whole and leaves the launches in flight alone.
+void recorded() {
+  vkv_pool* p = make_pool();
+  CHECK(kv_sched_set_overlap(p, 1) == VKV_OK);
+  CHECK(run(p, handle(0), 3, 2, kOne) == VKV_OK);
+  for (Call c : {kOne, kDecodeTwo, kPrefillMerged}) {
+    for (int max_inflight : {1, 2, 8}) {
+      {
+        std::lock_guard<std::mutex> lock(mu);
+        stream(handle(5))->capturing = stream(handle(9))->capturing = true;
+      }
+      const int before = launched;
+      CHECK(run(p, handle(5), 40, max_inflight, c) == VKV_OK);
+      CHECK(launched == before + 40 + c.n_tail);
+      {
+        std::lock_guard<std::mutex> lock(mu);
+        stream(handle(5))->capturing = stream(handle(9))->capturing = false;
+      }
+      CHECK(run(p, handle(0), 3, max_inflight, c) == VKV_OK);
+    }
+  }
+}
+
+// A launch that fails leaves the caller's stream behind everything that went to the second one.
+void failed_launch() {
+  for (Call c : {kDecodeTwo, kPrefillTwo}) {
+    vkv_pool* p = make_pool();
+    CHECK(kv_sched_set_overlap(p, 1) == VKV_OK);
+    gate(handle(9), false);
+    int32_t cursor = 0;
+    CHECK(run_slices(p, &cursor, 6, 8, handle(0), "check",
+                     [&](int32_t s, hipStream_t on) {
+                       if (s == 3) { set_error("slice 3"); return (int)VKV_E_HIP; }
+                       launch(p, on, 0);
+                       return (int)VKV_OK;
+                     }, 0, nullptr, false, c.may_overlap, c.end_events) == VKV_E_HIP);
+    CHECK(!std::strcmp(vkv_last_error(), "slice 3"));
+    std::atomic<bool> passed{false};
+    push(handle(0), [&]() { passed = true; });
+    std::this_thread::sleep_for(std::chrono::milliseconds(30));
+    CHECK(!passed);
+    gate(handle(9), true);
+    wait_idle(handle(0));
+    CHECK(passed && unfinished == 0);
+  }
+}
+
 }  // namespace
 
 // ---- the runtime functions the library calls ----
@@ -403,7 +450,8 @@ hipError_t hipEventSynchronize(hipEvent_t e) {
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"bound", bound}, {"lower_limit", lower_limit}, {"taking_turns", taking_turns}, {"yield_between", yield_between},
-      {"late_start", late_start}, {"failed_stream", failed_stream}, {"long_waits", long_waits}};
+      {"late_start", late_start}, {"failed_stream", failed_stream}, {"long_waits", long_waits},
+      {"recorded", recorded}, {"failed_launch", failed_launch}};
   if (argc != 2 || !checks.count(argv[1])) return 2;
   checks.at(argv[1])();
   std::printf("%s holds\n", argv[1]);

@@ -149,6 +149,62 @@ def test_static_call_in_a_graph_between_other_calls():
         c.close()
 
 
+@pytest.mark.parametrize("overlap", [False, True])
+def test_whole_layers_recorded_into_a_graph(overlap):
+    """Bind and run of a decode and of a prefill layer of more slices than max_inflight, one stream and two, recorded
+    and replayed with eager calls in between; the eager call right behind a replay finds its own count of launches."""
+    from gpu_util import DeviceCase
+    c = DeviceCase(synth.workload("offline_batch_small"), seed=16, host_pool=False)
+    try:
+        g, vkv = c.wl.geom, c.vkv
+        vkv.kv_sched_set_overlap(c.pool, overlap)
+        q, q_t = c.q_dev(0)
+        q_len = np.minimum(c.st.ctx_len, 300).astype(np.int32)
+        pq_t = torch.from_numpy(synth.hash_bf16_bits(np.arange(int(q_len.sum()) * g.num_q_heads * g.head_dim, dtype=np.int64), 4, 1)
+                                .reshape(-1, g.num_q_heads, g.head_dim).view(np.int16)).cuda()
+
+        def decode(out, bind=True):
+            if bind:
+                vkv.kv_attn_bind(c.pool, c.ws)
+            st, cur = vkv.kv_attn_run_layer(c.pool, 0, 0, q_t, c.tables_t, c.ws, out, max_inflight=2)
+            assert (st, cur) == (vkv.VKV_OK, info.n_slices)
+
+        def prefill(out, bind=True):
+            if bind:
+                vkv.kv_prefill_bind(c.pool, pws)
+            st, _ = vkv.kv_prefill_run_layer(c.pool, 0, 0, pq_t, c.tables_t, pws, out, max_inflight=2)
+            assert st == vkv.VKV_OK
+
+        info = c.plan(slice_bytes=2 << 20)
+        assert info.n_slices >= 13
+        pinfo = vkv.kv_prefill_plan(c.pool, c.st.ctx_len, q_len, 4 << 20, 512)
+        assert pinfo.n_slices > 2
+        pws = torch.empty(pinfo.workspace_bytes, dtype=torch.uint8, device="cuda:0")
+        want = torch.empty((c.wl.num_seqs, g.num_q_heads, g.head_dim), dtype=torch.float32, device="cuda:0")
+        pwant = torch.empty((pinfo.total_q, g.num_q_heads, g.head_dim), dtype=torch.float32, device="cuda:0")
+        decode(want)
+        prefill(pwant)
+        torch.cuda.synchronize()
+        for work, expected, binds in ((decode, want, False), (prefill, pwant, False), (decode, want, True), (prefill, pwant, True)):
+            work(torch.empty_like(expected))             # staging and workspace hold this plan
+            got, eager = torch.empty_like(expected), torch.empty_like(expected)
+            graph = torch.cuda.CUDAGraph()
+            torch.cuda.synchronize()
+            with torch.cuda.graph(graph):
+                work(got, binds)
+            for rep in range(4):
+                got.fill_(float("nan"))
+                eager.fill_(float("nan"))
+                graph.replay()
+                work(eager, False)
+                torch.cuda.synchronize()
+                assert torch.equal(got, expected) and torch.equal(eager, expected), (work.__name__, binds, rep)
+        vkv.kv_attn_check(c.pool, c.ws)
+        vkv.kv_prefill_check(c.pool, pws)
+    finally:
+        c.close()
+
+
 def _static_scratch(vkv):
     """The static call's 16 MiB array and the counters behind it as tensors, and the number of the last call."""
     import ctypes
