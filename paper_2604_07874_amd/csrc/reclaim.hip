@@ -245,7 +245,7 @@ int kv_reclaim_range(vkv_pool* p, int32_t lo, int32_t hi, int32_t* tables, int64
                          dim3(kCopyThreads), 0, cs, (u32x4*)p->cfg.base, (const int32_t*)remap_dev, first, block_vecs);
     he = hipGetLastError();
     if (he != hipSuccess) {
-      p->remap.n_flags = 0;   // no upload of this call is going to report
+      if (listed) p->remap.n_flags = 0;   // the upload was part of this launch; one of its own is under way and reports
       return fail(hip_fail(he, "kv_block_relocate launch"));
     }
     sent += (uint64_t)(j - i) * p->block_bytes;

@@ -83,6 +83,7 @@ void wait_idle(hipStream_t s) {
 hipStream_t handle(int n) { return (hipStream_t)(uintptr_t)(0x1000 + 64 * n); }
 
 bool drop_uploads = false;
+int kernels = 0, fail_kernel = 0;   // runtime launches so far; the one that fails, 0 = none
 int pause_us = 0;   // how long a launch takes, 0 = as short as it gets
 
 // what a slice kernel does for the scheduler
@@ -343,6 +344,34 @@ void failed_launch() {
   }
 }
 
+// A relocation whose copy cannot be launched: the remap's staging buffer is free again only if its upload was part of
+// that launch.
+void failed_copy() {
+  alignas(16) static char memory[64 * 4096];
+  for (bool listed : {true, false}) {
+    vkv_pool_config c{};
+    c.num_layers = c.num_q_heads = c.num_kv_heads = c.blocks_per_handle = 1;
+    c.head_dim = 64;
+    c.block_tokens = 16;
+    c.num_blocks = 64;
+    c.base = memory;
+    c.bytes = sizeof memory;
+    vkv_pool* p = nullptr;
+    CHECK(kv_pool_init(&c, &p) == VKV_OK && p->block_bytes == 4096);
+    const int32_t ids[3] = {1, 2, 3};
+    CHECK(kv_pool_adopt(p, ids, 3) == VKV_OK);
+    const hipStream_t s = handle(listed ? 1 : 2);
+    gate(s, false);
+    static int32_t remap[64], table[1] = {1};
+    fail_kernel = kernels + (listed ? 1 : 2);
+    CHECK(kv_reclaim_range(p, 0, 8, table, 1, listed ? 0 : 4096, 0, s, s, remap, 0, nullptr) == VKV_E_HIP);
+    CHECK(p->broken && p->remap.n_flags == (listed ? 0 : 1));
+    gate(s, true);
+    CHECK(stage_wait(p->remap) == VKV_OK && p->remap.n_flags == 0);
+    CHECK(listed || remap[1] != 1);
+  }
+}
+
 }  // namespace
 
 // ---- the runtime functions the library calls ----
@@ -364,6 +393,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 }
 // the kernels launched here: an upload by workgroups of 256, and one thread that stores a number
 hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size_t, hipStream_t s) {
+  if (++kernels == fail_kernel) return hipErrorInvalidConfiguration;
   if (block.x == 256) {
     const UploadShare u = *(UploadShare*)args[0];
     push(s, [u, grid]() {
@@ -379,7 +409,7 @@ hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size
   push(s, [word, value]() { __atomic_store_n(word, value, __ATOMIC_RELEASE); });
   return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() { return fail_kernel && kernels == fail_kernel ? hipErrorInvalidConfiguration : hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
   *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
   return hipSuccess;
@@ -451,7 +481,7 @@ int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"bound", bound}, {"lower_limit", lower_limit}, {"taking_turns", taking_turns}, {"yield_between", yield_between},
       {"late_start", late_start}, {"failed_stream", failed_stream}, {"long_waits", long_waits},
-      {"recorded", recorded}, {"failed_launch", failed_launch}};
+      {"recorded", recorded}, {"failed_launch", failed_launch}, {"failed_copy", failed_copy}};
   if (argc != 2 || !checks.count(argv[1])) return 2;
   checks.at(argv[1])();
   std::printf("%s holds\n", argv[1]);

@@ -1,4 +1,4 @@
-"""The slice scheduler (launches in flight, yields, decode and prefill taking turns) against a model of the GPU's
+"""The slice scheduler (launches in flight, yields, decode and prefill taking turns) and the uploads against a model of the GPU's
 streams: native/scheduler_check.cpp, linked with the library as it is built, in the place of the HIP runtime."""
 import os
 import subprocess
@@ -24,7 +24,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["bound", "lower_limit", "taking_turns", "yield_between", "late_start", "failed_stream",
-                                   "long_waits", "recorded", "failed_launch"])
+                                   "long_waits", "recorded", "failed_launch", "failed_copy"])
 def test_scheduler(program, check):
     try:
         res = subprocess.run([program, check], capture_output=True, text=True, timeout=30)
