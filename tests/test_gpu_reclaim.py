@@ -42,6 +42,40 @@ def compare_state(c, orc, lo_hi_released):
     assert np.array_equal(dev[keep], orc.pool[keep])
 
 
+@pytest.mark.parametrize("moves", [1, 447, 448, 449])
+@pytest.mark.parametrize("layers,kv_heads", [(5, 2), (3, 8), (16, 8), (17, 8), (32, 8)])
+def test_moves_on_both_sides_of_what_one_launch_can_carry(layers, kv_heads, moves):
+    """Up to 448 moves come with the launch itself, more through the remap on the device.  Blocks of 80 KiB (a ragged
+    second piece) and 192 KiB in 64 KiB pieces, of 1 MiB, 1088 KiB (a ragged last piece, so 64 KiB again) and 2 MiB in
+    128 KiB ones.  Every moved block, every other block outside the range, the tables and the remap, bit for bit."""
+    import paper_2604_07874_amd as vkv
+    elems, nb, hi = layers * 2 * kv_heads * 16 * 128, 1000, 460
+    gen = torch.Generator(device="cuda:0").manual_seed(layers * 1000 + moves)
+    pool_t = torch.randint(-32768, 32767, (nb, elems), dtype=torch.int16, device="cuda:0", generator=gen)
+    before = pool_t.clone()
+    rng = np.random.default_rng(moves)
+    inside = np.sort(rng.choice(hi, moves, replace=False)).astype(np.int32)
+    outside = hi + np.sort(rng.choice(nb - hi, 60, replace=False)).astype(np.int32)
+    live = np.concatenate([inside, outside])
+    pool = vkv.kv_pool_init(layers, kv_heads, kv_heads, 128, nb, 1, base=pool_t)
+    try:
+        vkv.kv_pool_adopt(pool, live)
+        want, _ = vkv.kv_reclaim_plan(pool, 0, hi, nb)
+        tables = torch.from_numpy(np.concatenate([live, [-1]]).astype(np.int32)).cuda()
+        remap_t = torch.empty(nb, dtype=torch.int32, device="cuda:0")
+        stats = vkv.kv_reclaim_range(pool, 0, hi, tables, remap_t)
+        assert (stats.blocks_moved, stats.n_chunks) == (moves, 1)
+        assert np.array_equal(remap_t.cpu().numpy(), want)
+        assert np.array_equal(tables.cpu().numpy(), np.concatenate([want[live], [-1]]))
+        dst = want[inside]
+        assert len(set(dst)) == moves and dst.min() >= hi
+        expected = before
+        expected[torch.from_numpy(dst).long().cuda()] = before[torch.from_numpy(inside).long().cuda()]
+        assert torch.equal(pool_t[hi:], expected[hi:])
+    finally:
+        vkv.kv_pool_destroy(pool)
+
+
 @pytest.mark.parametrize("name,seed,over", [
     ("tiny", 0, {}),
     ("tiny", 3, {"shared_prefix_blocks": 1, "ctx_dist": ("uniform", 40, 256)}),
