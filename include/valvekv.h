@@ -256,15 +256,17 @@ int paged_decode_attn_layer_static(vkv_pool* pool, int32_t layer, const void* q_
                                    float softmax_scale, void* stream);
 
 /* With enable != 0 the slice schedulers (kv_attn_run_layer, kv_prefill_run_layer)
- * may send every other slice of a layer to a second stream owned by the pool (a
- * decode layer of a few slices stays on one, where it is faster)
+ * send every other slice of a layer to a second stream owned by the pool
  * (created on first use, default priority), forked from and joined back into the
  * caller's stream inside the same call: the head of one launch fills the
  * compute units that the tail of the previous one leaves idle.  Ordering seen
  * by the caller is unchanged (work enqueued on `stream` before the call
  * precedes every slice; work enqueued after it follows every slice), results
  * are bit-identical, and at most max_inflight launches are unfinished as
- * before; it takes effect when max_inflight >= 2.  Off by default.  The first
+ * before; it takes effect when max_inflight >= 2.  With enable = 1 a decode layer
+ * is sent over two streams where that was measured to be faster: if it has 2 GB of
+ * K and V or more, in six slices or more that hold at least 120 MiB on average;
+ * with 2 every layer of two slices or more is.  Off by default.  The first
  * enabling call creates the stream (the device of the pool must be current);
  * make it before a second thread starts using the pool: kv_reclaim_range's
  * grace wait covers this stream too and reads its handle.

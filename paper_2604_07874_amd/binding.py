@@ -365,8 +365,9 @@ def kv_profile_read(pool, cap: int) -> np.ndarray:
     return buf[:n.value]
 
 
-def kv_sched_set_overlap(pool, enable: bool):
-    _check(lib.kv_sched_set_overlap(pool, 1 if enable else 0))
+def kv_sched_set_overlap(pool, enable: int):
+    """False or 0: one stream; True or 1: two where a layer gains by it; 2: two for every layer of two slices or more."""
+    _check(lib.kv_sched_set_overlap(pool, int(enable)))
 
 
 # ---- handle-backed pool memory ----------------------------------------------------

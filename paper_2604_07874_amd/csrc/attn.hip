@@ -458,6 +458,7 @@ int kv_attn_plan(vkv_pool* p, const int32_t* ctx, int32_t S, uint64_t slice_byte
   p->num_seqs = S;
   p->chunk_tokens = chunk_tokens;
   p->max_ctx_blocks = max_blocks;
+  p->kv_bytes = total;
   p->ws = workspace_layout((int64_t)p->work.size(), S, Hkv, p->G, D);
   p->has_plan = true;
   ++p->plan_gen;
@@ -565,7 +566,7 @@ int kv_attn_run_layer(vkv_pool* p, int32_t layer, int32_t* cursor, const void* q
                     [&](int32_t s, hipStream_t on) {
                       return launch_slice(p, layer, s, q, table, max_blk, workspace, out, scale, on, defer);
                     },
-                    0, nullptr, false, n_slices >= kDecodeOverlapMinSlices, true,
+                    0, nullptr, false, decode_overlaps(p->overlap, n_slices, p->kv_bytes), true,
                     defer ? std::function<int()>([&]() {
                       return launch_layer_merge(p, layer, q, table, max_blk, workspace, out, scale, hs);
                     }) : std::function<int()>());
@@ -665,7 +666,7 @@ int kv_sched_set_overlap(vkv_pool* p, int32_t enable) {
     if (!p->fork_ev) VKV_HIP(hipEventCreateWithFlags(&p->fork_ev, hipEventDisableTiming));
     if (!p->join_ev) VKV_HIP(hipEventCreateWithFlags(&p->join_ev, hipEventDisableTiming));
   }
-  p->overlap = enable != 0;
+  p->overlap = enable == 0 ? 0 : enable == 1 ? 1 : 2;
   return VKV_OK;
 }
 

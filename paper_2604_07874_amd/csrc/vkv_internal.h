@@ -35,12 +35,21 @@ constexpr int kMergeLdsBytes = 16 * 1024;   // LDS the last chunk may use for pe
 // a layer of at least this many slices merges its split sequences in one launch of its own after the last
 // slice (kv_attn_run_layer) instead of inside the slices
 constexpr int kDeferMergeMinSlices = 4;
-// A decode layer goes over two streams (kv_sched_set_overlap) from this many slices on.  The second stream costs a
-// layer 40-50 us (fork and join by event), the end of a launch that nothing fills about 11 us on one stream, where
-// kernels follow each other without a gap.  Measured, one stream against two: 4.4 GB layer in 5 slices of 1 GiB
-// 717 : 770 us, in 9 765 : 775, in 17 870 : 820; ten 18 GB layers in 17 slices each out of a 200 GiB pool 5837 : 6129-6254
-// GB/s; four 0.7 GB layers in 3 slices each 511 : 526 us, in 6 540 : 571.
-constexpr int kDecodeOverlapMinSlices = 12;
+// A decode layer goes over two streams (kv_sched_set_overlap 1) if it is long, in several slices, and they are not short.
+// The second stream fills the end of each launch.  It costs a layer a fork and a join by events, 40-50 us and more where
+// the layer is the only one of its step, and short slices suffer from the 25 us after which an event is seen.  Measured,
+// one stream against two, us a layer, ragged contexts, eight layers a step: 4.5 GB (8 kv heads) in 3 slices 726 : 729,
+// 5 728 : 703, 6 741 : 696, 9 807 : 700, 13 820 : 699; 2.2 GB (1 kv head) in 5 399 : 390, 6 419 : 385, 9 441 : 396, 13
+// 453 : 442, 18 of 122 MB 452 : 472; 4.5 GB (32 kv heads of 64) in 5 731 : 755, 6 721 : 723, 9 744 : 729, 18 791 : 732;
+// 1.1 GB (8 kv heads) in 6 208 : 214, 7 235 : 229, 9 of 118 MB 237 : 245, 13 of 81 MB 230 : 271.  One layer a step: 4.5 GB
+// (8 kv heads) in 5 732 : 782, 6 743 : 745, 7 710 : 780, 9 809 : 773, 13 822 : 764; 2.2 GB in 5 404 : 470, 9 445 : 470.
+// So what a model of many layers gains from five slices on, a step of one layer loses up to about eight: the line is six.
+constexpr int kDecodeOverlapMinSlices = 6;
+constexpr uint64_t kDecodeOverlapMinBytes = 2000000000ull, kDecodeOverlapMinSliceBytes = 120ull << 20;
+inline bool decode_overlaps(int overlap, int32_t n_slices, uint64_t kv_bytes) {
+  return overlap == 2 || (n_slices >= kDecodeOverlapMinSlices && kv_bytes >= kDecodeOverlapMinBytes &&
+                          kv_bytes / (uint64_t)n_slices >= kDecodeOverlapMinSliceBytes);
+}
 constexpr int kMaxChunkTokens = 2048;   // an item's block ids fit two registers per lane
 
 struct WorkItem {   // matches int4 on the device
@@ -205,6 +214,7 @@ struct vkv_pool {
   int32_t num_seqs = 0;
   int32_t chunk_tokens = 0;
   int32_t max_ctx_blocks = 0;                  // widest sequence in blocks
+  uint64_t kv_bytes = 0;                       // K and V of one layer
   std::vector<vkv::WorkItem> work;
   std::vector<int32_t> slice_start;
   std::vector<int32_t> seq_base;
@@ -244,7 +254,7 @@ struct vkv_pool {
   hipEvent_t inflight_ev[vkv::kMaxInflight] = {};   // behind the launch in the same place, where it is one for which events are used
   int inflight_head = 0, inflight_count = 0;
   // second stream for overlapping consecutive slices of one layer (created on first use)
-  bool overlap = false;
+  int overlap = 0;               // as given to kv_sched_set_overlap: 0, 1 or 2
   hipStream_t aux_stream = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   std::atomic<int> yield_flag{0};

@@ -372,6 +372,15 @@ void failed_copy() {
   }
 }
 
+// Which decode layers go over two streams: long ones cut into several slices that are worth a launch each, or as told.
+void overlap_rule() {
+  const uint64_t mib = 1ull << 20;
+  CHECK(!decode_overlaps(1, 5, 5000 * mib) && decode_overlaps(1, 6, 6000 * mib) && decode_overlaps(1, 9, 4264 * mib));
+  CHECK(decode_overlaps(1, 34, 34000 * mib) && decode_overlaps(1, 6, 2000000000) && !decode_overlaps(1, 6, 1999999999));
+  CHECK(decode_overlaps(1, 20, 2400 * mib) && !decode_overlaps(1, 20, 2400 * mib - 1) && !decode_overlaps(1, 7, 1000 * mib) && !decode_overlaps(1, 0, 0));
+  CHECK(decode_overlaps(2, 2, 2) && decode_overlaps(2, 14, 1000 * mib));
+}
+
 }  // namespace
 
 // ---- the runtime functions the library calls ----
@@ -481,7 +490,8 @@ int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"bound", bound}, {"lower_limit", lower_limit}, {"taking_turns", taking_turns}, {"yield_between", yield_between},
       {"late_start", late_start}, {"failed_stream", failed_stream}, {"long_waits", long_waits},
-      {"recorded", recorded}, {"failed_launch", failed_launch}, {"failed_copy", failed_copy}};
+      {"recorded", recorded}, {"failed_launch", failed_launch}, {"failed_copy", failed_copy},
+      {"overlap_rule", overlap_rule}};
   if (argc != 2 || !checks.count(argv[1])) return 2;
   checks.at(argv[1])();
   std::printf("%s holds\n", argv[1]);

@@ -79,7 +79,7 @@ def test_overlapped_slices_keep_stream_order_and_bits():
         assert info.n_slices >= 8
         q, q_t = c.q_dev(1)
         full = c.attention(1, q_t)
-        vkv.kv_sched_set_overlap(c.pool, True)
+        vkv.kv_sched_set_overlap(c.pool, 2)
         side = torch.cuda.Stream()
         out = torch.empty((c.wl.num_seqs, g.num_q_heads, g.head_dim), dtype=torch.float32, device="cuda:0")
         torch.cuda.synchronize()
@@ -120,7 +120,7 @@ def test_merge_is_repeatable_when_chunks_of_a_sequence_arrive_from_many_launches
         else:
             many = c.plan(slice_bytes=one.kv_bytes_per_layer // 3 + (1 << 16), chunk_tokens=128)
             assert many.n_slices == 3 and many.n_items == one.n_items
-        vkv.kv_sched_set_overlap(c.pool, True)
+        vkv.kv_sched_set_overlap(c.pool, 2)
         stream = torch.cuda.Stream()
         out = torch.empty((wl.num_seqs, g.num_q_heads, g.head_dim), dtype=torch.float32, device="cuda:0")
         for rep in range(20):

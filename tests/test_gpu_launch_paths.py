@@ -68,10 +68,10 @@ def test_bind_again_without_waiting_and_with_a_larger_plan():
 
 
 @pytest.mark.parametrize("max_inflight", [1, 2, 8])
-@pytest.mark.parametrize("overlap", [False, True])
+@pytest.mark.parametrize("overlap", [0, 2])
 def test_every_way_of_bounding_the_lead_gives_the_same_bits(max_inflight, overlap):
-    """One stream and two, reports of the start and of the end, layers on both sides of the number of slices from which
-    decode uses two streams, decode and prefill taking turns on one pool."""
+    """One stream and two, reports of the start and of the end, events, layers of one, few and many slices, decode and
+    prefill taking turns on one pool."""
     from gpu_util import DeviceCase
     c = DeviceCase(synth.workload("offline_batch_small"), seed=13, host_pool=False)
     try:
@@ -95,10 +95,10 @@ def test_every_way_of_bounding_the_lead_gives_the_same_bits(max_inflight, overla
         c.plan(slice_bytes=1 << 40)
         want = torch.from_numpy(c.attention(0, q_t)).cuda()
         _, pwant = prefill(1 << 40, 2)
-        counts = set()
+        counts = []
         for slice_bytes in (1 << 40, 16 << 20, 2 << 20):
             info = c.plan(slice_bytes=slice_bytes)
-            counts.add(info.n_slices >= 12)
+            counts.append(info.n_slices)
             out = torch.full_like(want, float("nan"))
             st, _ = vkv.kv_attn_run_layer(c.pool, 0, 0, q_t, c.tables_t, c.ws, out, max_inflight=max_inflight)
             assert st == vkv.VKV_OK
@@ -106,7 +106,7 @@ def test_every_way_of_bounding_the_lead_gives_the_same_bits(max_inflight, overla
             assert torch.equal(out, want), info.n_slices
             pinfo, pout = prefill(slice_bytes, max_inflight)
             assert torch.equal(pout, pwant), pinfo.n_slices
-        assert counts == {False, True}
+        assert counts[0] == 1 and 2 <= counts[1] < 12 <= counts[2]
     finally:
         c.close()
 
@@ -149,7 +149,7 @@ def test_static_call_in_a_graph_between_other_calls():
         c.close()
 
 
-@pytest.mark.parametrize("overlap", [False, True])
+@pytest.mark.parametrize("overlap", [0, 2])
 def test_whole_layers_recorded_into_a_graph(overlap):
     """Bind and run of a decode and of a prefill layer of more slices than max_inflight, one stream and two, recorded
     and replayed with eager calls in between; the eager call right behind a replay finds its own count of launches."""

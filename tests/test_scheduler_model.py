@@ -24,7 +24,8 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["bound", "lower_limit", "taking_turns", "yield_between", "late_start", "failed_stream",
-                                   "long_waits", "recorded", "failed_launch", "failed_copy"])
+                                   "long_waits", "recorded", "failed_launch", "failed_copy",
+                                   "overlap_rule"])
 def test_scheduler(program, check):
     try:
         res = subprocess.run([program, check], capture_output=True, text=True, timeout=30)
