@@ -298,3 +298,38 @@ def test_prefill_items_of_every_small_group_count(name, groups):
         assert err <= TOL, err
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("ctx", [8193, 8225, 16352, 16353, 16383, 16384, 16385, 32768])
+@pytest.mark.parametrize("heads", [(8, 1), (32, 8)])
+def test_prefill_items_up_to_the_longest(heads, ctx):
+    """Items of 257 to 512 groups (16384 tokens, the limit): all 17 windows of block addresses, the last entries of their
+    array, a second chunk of one token; two prompts whose newest rows end at the item's end.  Each row by its own
+    2-norm: weights rounded to bf16 differ by 2^-9 at most, 0.0011 in the mean square, so 0.005; one wrong block of
+    16384 tokens would change a row by 0.04."""
+    from dataclasses import replace
+    from gpu_util import DeviceCase, layout_of
+    wl = synth.workload("llama70b_tp8_small", ctx_dist=("uniform", ctx, ctx), num_seqs=2, reclaim_blocks=64)
+    nb = -(-2 * -(-ctx // 16) * 5 // 4 // 64) * 64 + 64
+    wl = replace(wl, geom=replace(wl.geom, num_layers=1, num_q_heads=heads[0], num_kv_heads=heads[1], num_blocks=nb))
+    c = DeviceCase(wl, seed=ctx)
+    try:
+        g, vkv = wl.geom, c.vkv
+        assert list(c.st.ctx_len) == [ctx, ctx]
+        q_len = np.array([41, 1], dtype=np.int32)
+        q_start = np.array([0, 41], dtype=np.int32)
+        q = synth.hash_bf16_bits(np.arange(42 * g.num_q_heads * g.head_dim, dtype=np.int64), ctx, 1)
+        q = q.reshape(-1, g.num_q_heads, g.head_dim)
+        info = vkv.kv_prefill_plan(c.pool, c.st.ctx_len, q_len, 64 << 20, 16384)
+        ws = torch.empty(info.workspace_bytes, dtype=torch.uint8, device="cuda:0")
+        vkv.kv_prefill_bind(c.pool, ws)
+        out = torch.full((info.total_q, g.num_q_heads, g.head_dim), float("nan"), dtype=torch.float32, device="cuda:0")
+        st, _ = vkv.kv_prefill_run_layer(c.pool, 0, 0, torch.from_numpy(q.view(np.int16)).cuda(), c.tables_t, ws, out)
+        assert st == vkv.VKV_OK
+        vkv.kv_prefill_check(c.pool, ws)
+        ref = paged_prefill_attention(c.pool_bits, layout_of(g), q, q_start, q_len, c.st.tables, c.st.ctx_len, 0)
+        diff = np.linalg.norm(out.cpu().numpy().astype(np.float64) - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+        print(f"largest relative error of a row {diff.max():.5f}")
+        assert diff.max() <= 5e-3, diff.max()
+    finally:
+        c.close()
