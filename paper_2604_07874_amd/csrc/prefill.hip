@@ -30,6 +30,8 @@
 // addresses wait in LDS (two readlanes each instead of loads, selects and 64-bit adds), four steps per trip turn
 // buffer offsets into immediates, and the step has about 140 instructions: 1350 cycles for two waves.  At that rate
 // the chip's clock falls to 1.8-1.9 GHz (a loop of nothing but these matrix instructions on random data runs at 1.6).
+// Counters over one layer of 64 sequences in 26 launches of 149 us: 1.93 GHz, matrix units busy 48 % of the cycles, 1.49
+// of 2 waves resident per SIMD (items start and end, launches run out), no bank conflict.
 // 32 prompts, the newest 2048 tokens of each: 2307 -> 1942 us; 4096 new tokens on 28k: 3007 -> 2182 us (945 TFLOP/s);
 // one prompt of 1901 tokens: 68.1 -> 48.9 us.
 #include "vkv_internal.h"
@@ -858,7 +860,7 @@ int kv_prefill_run_layer(vkv_pool* p, int32_t layer, int32_t* cursor, const void
                     (int32_t)p->pf.merge_start.size() - 1,
                     [&](int32_t step) { return pf_launch_merge(p, step, workspace, out, hs); }, !p->pf.merge_tiles.empty(),
                     true,   // two streams: few, long items per slice, 2300 : 1940 us in 20 slices, no worse in 3
-                    false);
+                    false);  // ends reported: events 2-3 % faster in 3 to 5 slices of 400-670 items, as fast or up to 8 % slower elsewhere
 }
 
 int kv_prefill_check(vkv_pool* p, void* workspace, void* stream) {
